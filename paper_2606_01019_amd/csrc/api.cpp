@@ -51,7 +51,7 @@ constexpr int kMlpSingleMaxLayers = 32;      // deepest model whose verify gate/
 constexpr int kGemmMinBlocks = 192;          // GEMM workgroups below which the shape changes
 constexpr int kGemmSplitTarget = 256;        // workgroups a K split aims for (one per CU)
 constexpr int kGemmLongK = 256;              // K steps above which a K split pays for its reduction
-constexpr size_t kGemmPartBytes = 64u << 20;  // split-K partial tiles of one GEMM launch
+constexpr size_t kGemmPartBytes = 128u << 20;  // split-K partial tiles of one GEMM launch
 constexpr int kGemmCounters = 16384;          // split-K arrival counters (output blocks of one launch)
 constexpr int kFlowCounterWords = 1 << 17;    // one-launch step: error word and per-layer counters
 constexpr int kAoCounterBase = 64;             // attention + O launches: their counters after the error word
@@ -1325,49 +1325,22 @@ hvd_status forward(hvd_kv_s* k, const std::vector<SeqMeta>& seqs, std::vector<Ro
     a.M = M;
     a.part = sx.gemm_part;
     a.cnt = sx.gemm_cnt;
-    const int want = k->gemm_min_blocks;
     if (MT > k->skinny_max_mt && N % 128 == 0) {
-      // many rows: MFMA-tiled kernel, weights read once per XCD.  Of the
-      // tiles that give at least one workgroup per CU, 256 x 256 unless the
-      // 128-row tile pads the rows less (the padded rows' MFMA work is
-      // wasted: 848 rows run as 1024 or as 896); else 128 x 256 on 8 waves
-      // (one workgroup per CU, a six-slot operand ring), K-split to about
-      // 7/8 of a workgroup per CU unless 5/8 are there already; else
-      // 128 x 128 with a K split when even that leaves CUs idle.  Measured
-      // against 128 x 128: the 848-row batch 30.2 -> 29.3 ms (QKV unsplit,
-      // O and down split 2), the 32B multistep step 59.3 -> 57.1 ms (QKV
-      // split 2, O and down split 4)
-      static const int tile_bm[5] = {128, 128, 256, 256, 128}, tile_bn[5] = {128, 256, 256, 256, 256};
-      const int want_t = std::max(want, kCUs);
-      auto rb_of = [&](int t) { return (MT * 16 + tile_bm[t] - 1) / tile_bm[t]; };
-      auto fits = [&](int t) { return N % tile_bn[t] == 0 && N / tile_bn[t] * rb_of(t) >= want_t; };
+      // many rows: MFMA-tiled kernel, weights read once per XCD
       const bool mlp = epi == EPI_SILU || family == PF_DOWN;
       const bool single = lm_head && ((mlp && (epi == EPI_SILU ? k->mlp_single_gu : k->mlp_single_down)) ||
                                       (epi == EPI_LM && k->lm_single));
-      int tile = 0;
-      if (fits(2) && !(fits(1) && rb_of(1) * 128 < rb_of(2) * 256)) tile = 2;
-      // the hi + lo pair's 32 KB K steps leave the 4-wave 128 x 256 tile one
-      // workgroup per CU and a three-slot ring: the 8-wave tile's four slots
-      // serve it better (32B multistep, gate/up on the pair: 69.1 -> 67.3 ms)
-      else if (fits(1)) tile = single ? 1 : 4;
-      else if (N % tile_bn[4] == 0) tile = 4;
-      const bool forced = family <= PF_LM && k->tiled_force[family][0] && N % tile_bn[k->tiled_force[family][0] - 1] == 0;
-      if (forced) tile = k->tiled_force[family][0] - 1;
-      const int RB = (MT * 16 + tile_bm[tile] - 1) / tile_bm[tile];
-      const int nblk = N / tile_bn[tile] * RB;
-      int splits = 1;
-      if (forced) splits = std::max(1, std::min(k->tiled_force[family][1], a.KT / 32));
-      else if (tile == 4) {
-        if (nblk * 8 < want_t * 5) splits = std::max(1, std::min({4, (want_t * 7 / 8 + nblk - 1) / nblk, a.KT / 32}));
-      } else if (nblk < want_t) splits = std::max(1, std::min({4, (want_t + nblk - 1) / nblk, a.KT / 32}));
-      while (splits > 1 && (size_t)splits * RB * tile_bm[tile] * N * 4 > sx.gemm_part_bytes) --splits;
-      if (splits > 1 && nblk > kGemmCounters) splits = 1;  // one arrival counter per output tile
+      const int* force = k->tiled_force[family <= PF_LM ? family : 0];
+      const bool forced = family <= PF_LM && force[0] && N % kTileBN[force[0] - 1] == 0;
+      const TiledPlan plan = forced ? tiled_plan_forced(force[0] - 1, std::max(1, std::min(force[1], a.KT / 32)), MT, N,
+                                                        a.KT, sx.gemm_part_bytes)
+                                    : tiled_plan(MT, N, a.KT, single, kCUs, sx.gemm_part_bytes);
       if (epi == EPI_LM) {
-        lm_parts = N / tile_bn[tile];
+        lm_parts = N / 64;
         a.n_part = lm_parts;
       }
       ProfScope ps(k, family, (double)N * K * 2.0);
-      HIP_TRY(launch_gemm_tiled(epi, a, tile, !single, splits, sx.inv_rms, s));
+      HIP_TRY(launch_gemm_tiled(epi, a, plan, !single, sx.inv_rms, s));
       return HVD_OK;
     }
     // verify forwards: MLP and LM-head GEMMs on the hi activation part (as the

@@ -6,6 +6,7 @@
 #include <cstring>
 
 #include "host_state.h"
+#include "tiled_plan.h"
 
 using hvd::HostState;
 
@@ -57,4 +58,21 @@ int32_t hvdh_pages(void* h, int32_t id, int32_t* out, int32_t cap) {
   return n;
 }
 const char* hvdh_error(void* h) { return ((HostState*)h)->error().c_str(); }
+
+// Work plan of a large-batch GEMM: tile, workgroups, shared tiles, sharing workgroups
+void hvdh_tiled_plan(int32_t mtiles, int32_t N, int32_t KT, int32_t single, int32_t cus, int64_t part_bytes, int32_t* out4) {
+  const hvd::TiledPlan p = hvd::tiled_plan(mtiles, N, KT, single != 0, cus, (size_t)part_bytes);
+  out4[0] = p.tile;
+  out4[1] = p.n_wg;
+  out4[2] = p.n_shared;
+  out4[3] = p.n_sk;
+}
+// Run of worker w ([out4[0], out4[1])), the worker of the w-th workgroup, and the holder of step lo(w)
+void hvdh_tiled_run(int32_t n_shared, int32_t KT, int32_t n_sk, int32_t w, int32_t* out4) {
+  const hvd::SharedRuns r(n_shared, KT, n_sk);
+  out4[0] = r.lo(w);
+  out4[1] = r.lo(w + 1);
+  out4[2] = r.worker(w);
+  out4[3] = r.holder(r.lo(w));
+}
 }

@@ -5,6 +5,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "tiled_plan.h"
+
 namespace hvd {
 
 // Per-role kernel timing (profiling only): while a role's scope is open, its
@@ -318,10 +320,10 @@ hipError_t launch_gemm(int epi, const GemmArgs& a, int ns, int splits, int mbloc
                        hipStream_t s);
 // Large-batch GEMM (gemm_tiled.hip): tile 0 = 128 x 128, 1 = 128 x 256,
 // 2 = 256 x 256 (8 waves), 3 = 256 x 256 (4 waves), 4 = 128 x 256 (8 waves)
-// (rows x columns); hi_lo false = the hi activation part
-// alone; K split `splits` ways; inv_rms is a per-row scratch vector
-// (computed here for normalised inputs).
-hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, int tile, bool hi_lo, int splits, float* inv_rms,
+// (rows x columns), work dealt out by the plan; hi_lo false = the hi
+// activation part alone; inv_rms is a per-row scratch vector (computed here
+// for normalised inputs).
+hipError_t launch_gemm_tiled(int epi, const GemmArgs& a, const TiledPlan& p, bool hi_lo, float* inv_rms,
                              hipStream_t s);
 // chunk: the plan's KV chunk length (picks the pages staged per sub-chunk);
 // rows_per_item: 64, 128 or 256 (256 for head_dim 128 only)

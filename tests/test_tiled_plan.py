@@ -1,0 +1,66 @@
+"""The work plan of the large-batch GEMMs (tiled_plan.h, through the host-only
+build): whatever the shape and the scratch it may use, the plan keeps what the
+kernel relies on -- every K step of a shared tile has exactly one worker, no
+run spans more than two tiles, partial slots are distinct and consecutive per
+tile, and the partial tiles fit the scratch."""
+
+import ctypes
+import os
+
+import numpy as np
+import pytest
+
+PKG = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_01019_amd")
+BM, BN = [128, 128, 256, 256, 128], [128, 256, 256, 256, 256]
+SHAPES = [(6144, 4096), (4096, 4096), (28672, 4096), (4096, 14336), (128256, 4096), (10240, 5120), (5120, 8192),
+          (55296, 5120), (5120, 27648), (152064, 5120), (768, 256), (256, 1024), (2048, 256), (128, 32), (384, 2048)]
+
+
+@pytest.fixture(scope="module")
+def lib():
+    path = os.path.join(PKG, "libhvd_host.so")
+    if not os.path.exists(path):
+        from paper_2606_01019_amd.build import build
+        build()
+    return ctypes.CDLL(path)
+
+
+@pytest.mark.parametrize("part_bytes", [0, 8 << 20, 128 << 20])
+@pytest.mark.parametrize("single", [0, 1])
+def test_plan_covers_every_k_step_once(lib, single, part_bytes):
+    out = (ctypes.c_int32 * 4)()
+    for N, K in SHAPES:
+        KT = K // 32
+        for mtiles in (9, 16, 17, 24, 32, 54, 128, 130):
+            lib.hvdh_tiled_plan(mtiles, N, KT, single, 256, ctypes.c_int64(part_bytes), out)
+            tile, n_wg, shared, n_sk = out
+            case = (N, K, mtiles, tile, n_wg, shared, n_sk)
+            assert N % BN[tile] == 0, case
+            T = -(-mtiles * 16 // BM[tile]) * (N // BN[tile])
+            assert 1 <= n_wg and 0 <= shared <= T and n_sk <= n_wg and (shared > 0) == (n_sk > 0), case
+            if not shared:
+                continue
+            assert shared <= n_sk <= shared * KT, case
+            assert (n_sk + shared) * BM[tile] * BN[tile] * 4 <= part_bytes, case
+            done = np.zeros(shared * KT, dtype=np.int32)
+            workers, slots = set(), {}
+            for w in range(n_sk):
+                lib.hvdh_tiled_run(shared, KT, n_sk, w, out)
+                lo, hi, worker, holder = out
+                assert lo < hi and holder == w, case
+                workers.add(worker)
+                done[lo:hi] += 1
+                tiles = range(lo // KT, (hi - 1) // KT + 1)
+                assert len(tiles) <= 2, case
+                for t in tiles:
+                    assert w + t < n_sk + shared and slots.setdefault(w + t, t) == t, case
+                    slots[w + t] = t
+            assert (done == 1).all() and workers == set(range(n_sk)), case
+            assert len(slots) == sum((out_hi(lib, shared, KT, n_sk, w) for w in range(n_sk))), case
+
+
+def out_hi(lib, shared, KT, n_sk, w):
+    """Tiles that worker w's run touches."""
+    out = (ctypes.c_int32 * 4)()
+    lib.hvdh_tiled_run(shared, KT, n_sk, w, out)
+    return (out[1] - 1) // KT - out[0] // KT + 1
