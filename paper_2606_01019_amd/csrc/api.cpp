@@ -35,14 +35,12 @@ hvd_status set_err(hvd_status s, const std::string& m) {
   } while (0)
 
 constexpr size_t kAlign = 256;
-// Prefill chunk: rows whose query rows per kv head (rows x group) come to
-// 2048, between 128 and 512 rows (measured: 512 rows for the 8B shape,
-// group 4, above 256 and 1024; 256 for the 32B shape, group 8, above 512).
-// HVD_OPT_PREFILL_ROWS overrides it per handle (up to this size).
-int prefill_rows(const hvd_config& c) {
-  const int G = c.n_q_heads / c.n_kv_heads;
-  return std::max(128, std::min(512, 2048 / G));
-}
+// Rows of a prefill chunk, at most: 2048 fill the CUs with whole tiles in
+// every GEMM of the 8B shape (512-row chunks split K in three of four and
+// re-read the weights four times as often).  HVD_OPT_PREFILL_ROWS overrides
+// it per handle.
+constexpr int kPrefillRows = 2048;
+int prefill_rows(const hvd_config& c) { return std::min(kPrefillRows, (c.max_pos + 15) / 16 * 16); }
 // Up to 8 row tiles (128 rows) the skinny kernel in row blocks of <= 4
 // tiles beats the tiled kernel (measured: 65-row verifies and 128-row
 // prefill chunks of the 8B shape)
@@ -454,8 +452,10 @@ size_t carve_kv(hvd_kv_s* k, const hvd_config& c, int max_seqs, int n_pages, voi
   k->Ahi = cv.take<uint16_t>(Mp * F + pad);
   k->Alo = cv.take<uint16_t>(Mp * F + pad);
   k->n_part_lm = c.vocab / 16;  // LM-head partials per row (upper bound: one per strip)
-  k->lm_val = cv.take<float>(Mp * k->n_part_lm);
-  k->lm_idx = cv.take<int32_t>(Mp * k->n_part_lm);
+  // (verify rows only: prefill has no LM head)
+  const size_t Mv = ((size_t)max_seqs * (c.max_draft + 1) + 15) / 16 * 16;
+  k->lm_val = cv.take<float>(Mv * k->n_part_lm);
+  k->lm_idx = cv.take<int32_t>(Mv * k->n_part_lm);
   k->gemm_part = cv.take<float>(kGemmPartBytes / 4);
   k->gemm_cnt = cv.take<uint32_t>(kGemmCounters);
   k->inv_rms = cv.take<float>(Mp);
@@ -1392,6 +1392,8 @@ hvd_status forward(hvd_kv_s* k, const std::vector<SeqMeta>& seqs, std::vector<Ro
       a.rope = m->rope;
       if (hvd_status st = gemm(EPI_QKV, a, qd + 2 * kvd, D, PF_QKV); st != HVD_OK) return st;
     }
+    // prefill leaves K/V only: nothing reads what follows in the last layer
+    if (!lm_head && l + 1 == c.n_layers) break;
     if (attn_o) {
       const Plan& pl = plans[1];
       AttnOArgs ao{};
@@ -1677,7 +1679,12 @@ extern "C" hvd_status hvd_prefill(hvd_model m, hvd_kv k, int32_t seq_id, const i
   if (k->m != m) return set_err(HVD_ERR_ARG, "kv handle belongs to another model");
   if (hvd_status st = from_host(k->hs->begin_prefill(seq_id, tokens, n), k); st != HVD_OK) return st;
   const int body = n - 1;
-  const int chunk_rows = k->prefill_rows ? k->prefill_rows : prefill_rows(m->cfg);
+  // the fewest chunks, of about equal size (a multiple of the GEMMs' 128-row tiles)
+  int chunk_rows = k->prefill_rows;
+  if (!chunk_rows) {
+    const int most = prefill_rows(m->cfg), n_chunks = std::max(1, (body + most - 1) / most);
+    chunk_rows = std::min(most, ((body + n_chunks - 1) / n_chunks + 127) / 128 * 128);
+  }
   for (int s0 = 0; s0 < body; s0 += chunk_rows) {
     const int cnt = std::min(chunk_rows, body - s0);
     std::vector<SeqMeta> seqs{{seq_id, s0, cnt - 1, 0}};
