@@ -298,7 +298,7 @@ hvd_status hvd_profile_read(hvd_kv kv, int32_t family, double* ms, int64_t* laun
  *   aims for.  HVD_OPT_ATTN_MAX_NP (16): most KV pages one attention
  *   sub-chunk stages (power of two, 2..16).  HVD_OPT_SKINNY_MAX_MT (8): row
  *   tiles above which GEMMs take the MFMA-tiled kernel.  HVD_OPT_NS8_MT3 (1):
- *   8-strip skinny blocks at three and four single-pass row tiles.
+ *   8-strip GEMM blocks at three and four row tiles.
  *   HVD_OPT_PREFILL_ROWS (0 = policy): prefill chunk rows, a multiple of 16.
  * HVD_OPT_GEMM_SHAPE + f, f = 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head:
  *   skinny GEMM shape of that GEMM, strips * 100 + K splits (0 = policy).

@@ -316,6 +316,8 @@ hipError_t launch_embed(const EmbedArgs& a, hipStream_t s);
 // to finish reduces (a.part, a.cnt).
 // hi_lo false: the hi activation part alone (honoured for the residual and
 // SiLU GEMMs at 3-4 row tiles; other shapes keep the pair)
+hipError_t launch_gemm_mid(int epi, const GemmArgs& a, int strips, int splits, int mblocks, int mt_block, bool hi_lo,
+                           hipStream_t s);
 hipError_t launch_gemm(int epi, const GemmArgs& a, int ns, int splits, int mblocks, int mt_block, bool hi_lo,
                        hipStream_t s);
 // Large-batch GEMM (gemm_tiled.hip): tile 0 = 128 x 128, 1 = 128 x 256,
