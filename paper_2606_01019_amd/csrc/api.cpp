@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/hvd.h"
+#include "attn_order.h"
 #include "host_state.h"
 #include "kernels.h"
 
@@ -709,7 +710,7 @@ struct Plan {
 // to fill the GPU; at most part_rows_free partial-buffer rows.
 bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<SeqMeta>& seqs,
                     const std::vector<int>& members, int min_items, int rpi, size_t part_rows_free, Plan& p,
-                    int max_items = 0) {
+                    int max_items, bool by_length) {
   const int G = c.n_q_heads / c.n_kv_heads;
   struct Unit { int b, g, rg, keys; };
   auto item = [&](const Unit& u, int ci, int nch, int part, int chunk) {
@@ -772,14 +773,16 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
     chunk = 32;
     while (chunk < (1 << 20) && n_items_at(chunk) > max_items) chunk *= 2;
   }
-  // Several row groups of one (sequence, kv head) read the same K/V chunks.
-  // Their items go 8 grid positions apart, next to each other in dispatch
-  // order: the same XCD under round-robin dispatch, at nearly the same time,
-  // so a chunk comes from HBM once and from that XCD's L2 for the others.
-  // Per (sequence, kv head) with n_rg > 1 row groups, chunks in runs of 8:
-  // item (run position j, row group r) at run base + 8r + j, a no-op item
-  // (k = -1) where a row group has fewer chunks.  Partial slots and merge
-  // entries follow the units in order, as with one row group.
+  // Order of the items (attn_order.h): eight interleaved queues, one per XCD, the
+  // longest items first.  The row groups of one (sequence, kv head) that read a
+  // chunk share a queue, hence an XCD: the chunk comes from HBM once and from
+  // that XCD's L2 for the others.  In unit order the last workgroups of a
+  // launch were as long as any, and half of the CUs waited for them: attention
+  // of a 2048-token prefill chunk 180 -> 147 us per layer, of the 848-row batch's
+  // 256-row items 143 -> 109, 384-row items of the 32B widths at context 8192
+  // 77 -> 57.  64-row items (two per CU, of nearly equal length) keep the unit
+  // order, as do the device-wide launches of flow.hip and attn_o.hip.
+  // Partial slots and merge entries follow the units in either case.
   AttnItem none{};
   none.k = -1;
   std::vector<int> nch_u, slot_u;
@@ -799,26 +802,18 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
         slots += nch;
       }
     }
-    for (size_t i0 = 0; i0 < units.size();) {
-      size_t i1 = i0 + 1;  // units [i0, i1): the row groups of one (sequence, kv head)
-      while (i1 < units.size() && units[i1].b == units[i0].b && units[i1].g == units[i0].g) ++i1;
-      auto emit = [&](size_t i, int ci) {
-        const int nch = nch_u[i];
-        if (ci >= nch) p.items.push_back(none);
-        else p.items.push_back(nch == 1 ? item(units[i], 0, 1, -1, chunk) : item(units[i], ci, nch, slot_u[i] + ci, chunk));
-      };
-      if (i1 - i0 == 1) {
-        for (int ci = 0; ci < nch_u[i0]; ++ci) emit(i0, ci);
-      } else {
-        int max_nch = 0;
-        for (size_t i = i0; i < i1; ++i) max_nch = std::max(max_nch, nch_u[i]);
-        for (int c0 = 0; c0 < max_nch; c0 += 8) {
-          const int run = std::min(8, max_nch - c0);
-          for (size_t i = i0; i < i1; ++i)
-            for (int j = 0; j < run; ++j) emit(i, c0 + j);
-        }
-      }
-      i0 = i1;
+    std::vector<AttnPiece> pieces;
+    for (size_t i = 0; i < units.size(); ++i) {
+      const int stream = units[i].b * c.n_kv_heads + units[i].g;
+      for (int ci = 0; ci < nch_u[i]; ++ci)
+        pieces.push_back({stream, (int)i, ci, std::min(units[i].keys, (ci + 1) * chunk) - ci * chunk});
+    }
+    if (by_length) pieces = attn_order(pieces);
+    for (const AttnPiece& q : pieces) {
+      const int nch = q.unit < 0 ? 0 : nch_u[q.unit];
+      p.items.push_back(nch == 0   ? none
+                        : nch == 1 ? item(units[q.unit], 0, 1, -1, chunk)
+                                   : item(units[q.unit], q.chunk, nch, slot_u[q.unit] + q.chunk, chunk));
     }
     if ((size_t)slots * rpi <= part_rows_free) {  // partial buffer rows
       p.part_rows = (size_t)slots * rpi;
@@ -924,7 +919,7 @@ hvd_status forward(hvd_kv_s* k, const std::vector<SeqMeta>& seqs, std::vector<Ro
     Plan& pl = plans[cl];
     if (!plan_attention(c, *k->hs, seqs, members[cl], flow ? k->flow_min_items : k->attn_min_items,
                         attn_o ? ao_rpi : kClassRows[cl], sx.part_rows - part_used, pl,
-                        attn_o ? ao_attn_wgs : 0))
+                        attn_o ? ao_attn_wgs : 0, !flow && !attn_o && kClassRows[cl] > kAttnRows / 2))
       return set_err(HVD_ERR_OOM, "attention partial slots exhausted");
     pl.part_base = part_used;
     part_used += pl.part_rows;

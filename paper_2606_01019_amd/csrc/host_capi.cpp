@@ -6,6 +6,7 @@
 #include <cstring>
 
 #include "host_state.h"
+#include "attn_order.h"
 #include "tiled_plan.h"
 
 using hvd::HostState;
@@ -74,5 +75,19 @@ void hvdh_tiled_run(int32_t n_shared, int32_t KT, int32_t n_sk, int32_t w, int32
   out4[1] = r.lo(w + 1);
   out4[2] = r.worker(w);
   out4[3] = r.holder(r.lo(w));
+}
+// Launch order of attention items [n][4] (stream, unit, chunk, keys); returns the
+// count, no-op pieces (unit -1) included
+int32_t hvdh_attn_order(int32_t n, const int32_t* in, int32_t* out, int32_t cap) {
+  std::vector<hvd::AttnPiece> p(n);
+  for (int32_t i = 0; i < n; ++i) p[i] = {in[4 * i], in[4 * i + 1], in[4 * i + 2], in[4 * i + 3]};
+  p = hvd::attn_order(p);
+  for (size_t i = 0; i < p.size() && (int32_t)i < cap; ++i) {
+    out[4 * i] = p[i].stream;
+    out[4 * i + 1] = p[i].unit;
+    out[4 * i + 2] = p[i].chunk;
+    out[4 * i + 3] = p[i].keys;
+  }
+  return (int32_t)p.size();
 }
 }

@@ -1,0 +1,73 @@
+"""The launch order of attention items (attn_order.h, through the host-only
+build): every item appears exactly once whatever the batch, no-op entries never
+outnumber the items, the eight queues are balanced wherever single items allow
+it, each queue runs its longest items first, and the row groups of one chunk
+share a queue where bundles can be balanced."""
+
+import ctypes
+import os
+
+import numpy as np
+import pytest
+
+PKG = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_01019_amd")
+
+
+@pytest.fixture(scope="module")
+def lib():
+    path = os.path.join(PKG, "libhvd_host.so")
+    if not os.path.exists(path):
+        from paper_2606_01019_amd.build import build
+        build()
+    return ctypes.CDLL(path)
+
+
+def order(lib, pieces):
+    a = np.ascontiguousarray(pieces, np.int32)
+    out = np.zeros((2 * len(a) + 8, 4), np.int32)
+    n = lib.hvdh_attn_order(len(a), a.ctypes.data_as(ctypes.c_void_p), out.ctypes.data_as(ctypes.c_void_p), len(out))
+    assert n <= 2 * len(a)
+    return out[:n]
+
+
+def pieces_of(seqs, heads, chunk):
+    """seqs: (row groups' key counts) per sequence -> (stream, unit, chunk, keys)."""
+    out, unit = [], 0
+    for b, groups in enumerate(seqs):
+        for g in range(heads):
+            for keys in groups:
+                out += [(b * heads + g, unit, c, min(keys, (c + 1) * chunk) - c * chunk) for c in range(-(-keys // chunk))]
+                unit += 1
+    return out
+
+
+CASES = {
+    "prefill": ([[64 * (i + 1) for i in range(32)]], 8, 1024),
+    "prefill, 4 heads": ([[64 * (i + 1) for i in range(32)]], 4, 1024),
+    "prefill, 1 head": ([[777 + 64 * i for i in range(32)]], 1, 512),
+    "mixed batch": ([[int(n)] for n in np.random.default_rng(0).integers(1024, 8192, 16)], 8, 1024),
+    "two row groups": ([[int(n), int(n) + 7] for n in np.random.default_rng(1).integers(64, 9000, 11)], 8, 512),
+    "one long, many short": ([[16384]] + [[70]] * 31, 8, 1024),
+    "few": ([[100]], 3, 32),
+    "one": ([[5]], 1, 64),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_order(lib, name):
+    pieces = pieces_of(*CASES[name])
+    out = order(lib, pieces)
+    real = [tuple(int(v) for v in r) for r in out if r[1] >= 0]
+    assert sorted(real) == sorted(pieces)
+    if len(out) == len(pieces) and len(out) % 8 and all(out[i][3] >= out[i + 1][3] for i in range(len(out) - 1)):
+        return  # plain length order: queues too uneven to interleave
+    queues = [[tuple(int(v) for v in r) for r in out[x::8] if r[1] >= 0] for x in range(8)]
+    loads = [sum(p[3] for p in q) for q in queues]
+    assert max(loads) * 8 <= sum(loads) * 9 // 8 + 8 * max(p[3] for p in pieces)
+    for q in queues:
+        assert all(q[i][3] >= q[i + 1][3] for i in range(len(q) - 1))
+    if name in ("prefill", "mixed batch", "two row groups"):
+        home = {}
+        for x, q in enumerate(queues):
+            for s, _, c, _ in q:
+                assert home.setdefault((s, c), x) == x
