@@ -780,8 +780,10 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
   // launch were as long as any, and half of the CUs waited for them: attention
   // of a 2048-token prefill chunk 180 -> 147 us per layer, of the 848-row batch's
   // 256-row items 143 -> 109, 384-row items of the 32B widths at context 8192
-  // 77 -> 57.  64-row items (two per CU, of nearly equal length) keep the unit
-  // order, as do the device-wide launches of flow.hip and attn_o.hip.
+  // 77 -> 57.  64-row items (two per CU) and the one row group of a single
+  // sequence, both of nearly equal length, keep the unit order (33-row tree at
+  // context 2048 4.38 against 4.49 ms, 65 rows at 16384 6.44 against 6.52), as do the
+  // device-wide launches of flow.hip and attn_o.hip.
   // Partial slots and merge entries follow the units in either case.
   AttnItem none{};
   none.k = -1;
@@ -808,7 +810,7 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
       for (int ci = 0; ci < nch_u[i]; ++ci)
         pieces.push_back({stream, (int)i, ci, std::min(units[i].keys, (ci + 1) * chunk) - ci * chunk});
     }
-    if (by_length) pieces = attn_order(pieces);
+    if (by_length && (members.size() > 1 || units.size() > (size_t)c.n_kv_heads)) pieces = attn_order(pieces);
     for (const AttnPiece& q : pieces) {
       const int nch = q.unit < 0 ? 0 : nch_u[q.unit];
       p.items.push_back(nch == 0   ? none
