@@ -574,10 +574,7 @@ template <int WY, int WX, int WM, int WN, int EPI, bool HI_LO>
 static hipError_t launch_t(const GemmArgs& a, const float* inv_rms, const TiledPlan& p, hipStream_t s) {
   const int BM = 32 * WM * WY, BN = 32 * WN * WX, NT = 64 * WY * WX;
   const int CB = a.NT * 16 / BN, RB = (a.MTtot * 16 + BM - 1) / BM;
-  // the kernel's assumptions: a shared run never spans more than two tiles,
-  // and every shared K step has a workgroup
-  if (p.n_wg < 1 || p.n_shared < 0 || p.n_shared > CB * RB || p.n_sk > p.n_wg || (p.n_shared > 0) != (p.n_sk > 0) ||
-      (p.n_sk > 0 && (p.n_sk < p.n_shared || p.n_shared * (int64_t)a.KT < p.n_sk || p.n_shared * (int64_t)a.KT > INT32_MAX)))
+  if (!tiled_plan_ok(p, CB * RB, a.KT))
     return hipErrorInvalidValue;
   hvd_launch((gemm_tiled<WY, WX, WM, WN, EPI, HI_LO>), dim3(p.n_wg), dim3(NT), 0, s, a, inv_rms, RB, CB, p.n_shared,
              p.n_sk);

@@ -68,6 +68,9 @@ void hvdh_tiled_plan(int32_t mtiles, int32_t N, int32_t KT, int32_t single, int3
   out4[2] = p.n_shared;
   out4[3] = p.n_sk;
 }
+int hvdh_tiled_plan_ok(int32_t tile, int32_t n_wg, int32_t n_shared, int32_t n_sk, int32_t T, int32_t KT) {
+  return hvd::tiled_plan_ok(hvd::TiledPlan{tile, n_wg, n_shared, n_sk}, T, KT);
+}
 // Run of worker w ([out4[0], out4[1])), the worker of the w-th workgroup, and the holder of step lo(w)
 void hvdh_tiled_run(int32_t n_shared, int32_t KT, int32_t n_sk, int32_t w, int32_t* out4) {
   const hvd::SharedRuns r(n_shared, KT, n_sk);

@@ -49,6 +49,17 @@ struct SharedRuns {
   }
 };
 
+// What the kernels assume of a plan for T tiles of KT K steps: every shared K
+// step has a workgroup, a run spans at most two tiles, and no run covers a whole
+// tile -- gemm_tiled takes a part that does for a whole tile of its own and
+// publishes nothing, and tiled_finish would sum the slot it left unwritten.
+inline bool tiled_plan_ok(const TiledPlan& p, int T, int KT) {
+  const int64_t steps = (int64_t)p.n_shared * KT;
+  if (p.n_wg < 1 || p.n_shared < 0 || p.n_shared > T || p.n_sk > p.n_wg || (p.n_shared > 0) != (p.n_sk > 0)) return false;
+  if (!p.n_shared) return true;
+  return steps >= p.n_sk && steps <= INT32_MAX && (steps + p.n_sk - 1) / p.n_sk < KT;
+}
+
 // Bytes of partial tiles the plan publishes.
 inline size_t tiled_partial_bytes(const TiledPlan& p) {
   return p.n_shared ? (size_t)(p.n_sk + p.n_shared) * kTileBM[p.tile] * kTileBN[p.tile] * 4 : 0;
@@ -109,6 +120,7 @@ inline TiledPlan tiled_plan(int mtiles, int N, int KT, bool single, int cus, siz
     const int n_wg = T < cus ? 0 : cus;  // (0: as many as share)
     auto shared = [&](int n_sk, double factor) {
       const TiledPlan p{t, std::max(n_wg, n_sk), rest, n_sk};
+      if (!tiled_plan_ok(p, T, KT)) return;
       const int steps = (int)(((int64_t)rest * KT + n_sk - 1) / n_sk);
       consider(p, kLaunch + whole + run(steps, n_sk) * factor + kFinish + tiled_partial_bytes(p) / kPartRate + epi);
     };

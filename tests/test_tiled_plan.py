@@ -37,17 +37,18 @@ def test_plan_covers_every_k_step_once(lib, single, part_bytes):
             case = (N, K, mtiles, tile, n_wg, shared, n_sk)
             assert N % BN[tile] == 0, case
             T = -(-mtiles * 16 // BM[tile]) * (N // BN[tile])
+            assert lib.hvdh_tiled_plan_ok(tile, n_wg, shared, n_sk, T, KT), case
             assert 1 <= n_wg and 0 <= shared <= T and n_sk <= n_wg and (shared > 0) == (n_sk > 0), case
             if not shared:
                 continue
-            assert shared <= n_sk <= shared * KT, case
+            assert shared < n_sk <= shared * KT, case
             assert (n_sk + shared) * BM[tile] * BN[tile] * 4 <= part_bytes, case
             done = np.zeros(shared * KT, dtype=np.int32)
             workers, slots = set(), {}
             for w in range(n_sk):
                 lib.hvdh_tiled_run(shared, KT, n_sk, w, out)
                 lo, hi, worker, holder = out
-                assert lo < hi and holder == w, case
+                assert lo < hi < lo + KT and holder == w, case  # a part, never a whole tile
                 workers.add(worker)
                 done[lo:hi] += 1
                 tiles = range(lo // KT, (hi - 1) // KT + 1)
@@ -64,3 +65,27 @@ def out_hi(lib, shared, KT, n_sk, w):
     out = (ctypes.c_int32 * 4)()
     lib.hvdh_tiled_run(shared, KT, n_sk, w, out)
     return (out[1] - 1) // KT - out[0] // KT + 1
+
+
+@pytest.mark.parametrize("plan, T, KT, ok", [
+    ((4, 192, 96, 192), 96, 128, True),
+    ((4, 256, 128, 256), 896, 128, True),
+    ((4, 256, 140, 256), 140, 256, True),
+    ((4, 300, 0, 0), 300, 16, True),
+    ((4, 40, 40, 40), 40, 64, False),      # one worker per shared tile
+    ((4, 256, 255, 256), 511, 128, False),  # 127.5 steps per worker: the first 128 runs are whole tiles
+    ((4, 256, 254, 256), 510, 128, True),   # 127 steps each
+    ((4, 8, 1, 8), 1, 7, False),            # more workers than steps
+    ((4, 8, 2, 16), 2, 64, False),          # more workers than workgroups
+    ((4, 8, 3, 8), 2, 64, False),           # more shared tiles than tiles
+    ((4, 8, 2, 0), 2, 64, False),
+])
+def test_plans_the_kernels_cannot_run_are_refused(lib, plan, T, KT, ok):
+    """A run that covers a whole tile would be finished twice, once from a partial
+    slot that nothing wrote: the launcher refuses such plans."""
+    assert bool(lib.hvdh_tiled_plan_ok(*plan, T, KT)) == ok
+    if ok and plan[2]:
+        out = (ctypes.c_int32 * 4)()
+        for w in range(plan[3]):
+            lib.hvdh_tiled_run(plan[2], KT, plan[3], w, out)
+            assert out[1] - out[0] < KT
