@@ -79,6 +79,10 @@ void hvdh_tiled_run(int32_t n_shared, int32_t KT, int32_t n_sk, int32_t w, int32
   out4[2] = r.worker(w);
   out4[3] = r.holder(r.lo(w));
 }
+// Partial slot of worker w's part of shared tile t
+int32_t hvdh_tiled_slot(int32_t n_shared, int32_t KT, int32_t n_sk, int32_t w, int32_t t) {
+  return hvd::SharedRuns(n_shared, KT, n_sk).slot0(w) + t;
+}
 // Launch order of attention items [n][4] (stream, unit, chunk, keys); returns the
 // count, no-op pieces (unit -1) included
 int32_t hvdh_attn_order(int32_t n, const int32_t* in, int32_t* out, int32_t cap) {

@@ -29,23 +29,31 @@ struct TiledPlan {
 
 // The shared K steps, counted through the shared tiles in order (tile t holds
 // steps t KT .. t KT + KT - 1), and the runs they are dealt out in: worker w
-// has steps [lo(w), lo(w + 1)), and its part of shared tile t goes to partial
-// slot w + t (distinct, since runs are contiguous, and consecutive per tile).
+// has steps [lo(w), lo(w + 1)).  With as many workers for every tile (parts > 0)
+// each tile's steps are cut alike and worker w's part goes to partial slot w.
+// Otherwise a run may span two tiles, and its part of shared tile t goes to slot
+// w + t (distinct, since runs are contiguous, and consecutive per tile).
 struct SharedRuns {
-  int q, r, n_shared, n_sk;
-  HVD_HOST_DEVICE SharedRuns(int n_shared_, int KT, int n_sk_)
-      : q(n_sk_ ? n_shared_ * KT / n_sk_ : 0), r(n_sk_ ? n_shared_ * KT % n_sk_ : 0), n_shared(n_shared_), n_sk(n_sk_) {}
-  HVD_HOST_DEVICE int lo(int w) const { return w * q + (w < r ? w : r); }
+  int KT, q, r, n_shared, n_sk, parts;
+  HVD_HOST_DEVICE SharedRuns(int n_shared_, int KT_, int n_sk_)
+      : KT(KT_), q(n_sk_ ? n_shared_ * KT_ / n_sk_ : 0), r(n_sk_ ? n_shared_ * KT_ % n_sk_ : 0), n_shared(n_shared_),
+        n_sk(n_sk_), parts(n_sk_ && n_sk_ % n_shared_ == 0 ? n_sk_ / n_shared_ : 0) {}
+  HVD_HOST_DEVICE int lo(int w) const {
+    return parts ? w / parts * KT + w % parts * KT / parts : w * q + (w < r ? w : r);
+  }
   // the worker whose run holds a step
   HVD_HOST_DEVICE int holder(int step) const {
+    if (parts) return step / KT * parts + ((step % KT + 1) * parts - 1) / KT;
     const int cut = r * (q + 1);
     return step < cut ? step / (q + 1) : r + (step - cut) / q;
   }
+  // worker w's partial slot of shared tile t is slot0(w) + t
+  HVD_HOST_DEVICE int slot0(int w) const { return parts ? w - w / parts : w; }
   // worker of the l-th workgroup in XCD order: with a uniform split, the same
   // K range of neighbouring tiles goes to neighbours, which share its
   // operands in their L2 (328 rows x 5120 columns, K 27648: 228 -> 218 us)
   HVD_HOST_DEVICE int worker(int l) const {
-    return n_sk % n_shared == 0 ? l % n_shared * (n_sk / n_shared) + l / n_shared : l;
+    return parts ? l % n_shared * parts + l / n_shared : l;
   }
 };
 
@@ -60,9 +68,12 @@ inline bool tiled_plan_ok(const TiledPlan& p, int T, int KT) {
   return steps >= p.n_sk && steps <= INT32_MAX && (steps + p.n_sk - 1) / p.n_sk < KT;
 }
 
-// Bytes of partial tiles the plan publishes.
+// Bytes of partial slots the plan needs.  An even split needs one per worker:
+// 8 MiB (hvd_verify_noalloc) then hold a two-way split of 256 rows x 4096 columns,
+// 64 workgroups instead of 32 (4 layers of the 8B widths, 130 rows: 2.72 -> 1.97 ms).
 inline size_t tiled_partial_bytes(const TiledPlan& p) {
-  return p.n_shared ? (size_t)(p.n_sk + p.n_shared) * kTileBM[p.tile] * kTileBN[p.tile] * 4 : 0;
+  if (!p.n_shared) return 0;
+  return (size_t)(p.n_sk + (p.n_sk % p.n_shared ? p.n_shared : 0)) * kTileBM[p.tile] * kTileBN[p.tile] * 4;
 }
 
 // `splits`-way K split of every tile (1: whole tiles), for tuning overrides.
@@ -122,7 +133,7 @@ inline TiledPlan tiled_plan(int mtiles, int N, int KT, bool single, int cus, siz
       const TiledPlan p{t, std::max(n_wg, n_sk), rest, n_sk};
       if (!tiled_plan_ok(p, T, KT)) return;
       const int steps = (int)(((int64_t)rest * KT + n_sk - 1) / n_sk);
-      consider(p, kLaunch + whole + run(steps, n_sk) * factor + kFinish + tiled_partial_bytes(p) / kPartRate + epi);
+      consider(p, kLaunch + whole + run(steps, n_sk) * factor + kFinish + (double)(n_sk + rest) * kTileBM[t] * kTileBN[t] * 4 / kPartRate + epi);
     };
     for (int s = 2; s <= 16 && rest * s <= cus && KT / s >= kMinRun; ++s) shared(rest * s, 1.0);
     const int n_sk = (int)std::min<int64_t>(cus, (int64_t)rest * KT / kMinRun);

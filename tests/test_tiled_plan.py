@@ -42,7 +42,8 @@ def test_plan_covers_every_k_step_once(lib, single, part_bytes):
             if not shared:
                 continue
             assert shared < n_sk <= shared * KT, case
-            assert (n_sk + shared) * BM[tile] * BN[tile] * 4 <= part_bytes, case
+            n_slots = n_sk + (shared if n_sk % shared else 0)
+            assert n_slots * BM[tile] * BN[tile] * 4 <= part_bytes, case
             done = np.zeros(shared * KT, dtype=np.int32)
             workers, slots = set(), {}
             for w in range(n_sk):
@@ -54,9 +55,16 @@ def test_plan_covers_every_k_step_once(lib, single, part_bytes):
                 tiles = range(lo // KT, (hi - 1) // KT + 1)
                 assert len(tiles) <= 2, case
                 for t in tiles:
-                    assert w + t < n_sk + shared and slots.setdefault(w + t, t) == t, case
-                    slots[w + t] = t
+                    slot = lib.hvdh_tiled_slot(shared, KT, n_sk, w, t)
+                    assert 0 <= slot < n_slots and slot not in slots, case
+                    slots[slot] = t
+                if n_sk % shared == 0:  # an even split: one tile per worker, cut alike
+                    i = w % (n_sk // shared)
+                    assert len(tiles) == 1 and lo % KT == i * KT // (n_sk // shared), case
             assert (done == 1).all() and workers == set(range(n_sk)), case
+            for t in range(shared):  # consecutive per tile, as the finishing kernel reads them
+                mine = sorted(s for s, u in slots.items() if u == t)
+                assert mine == list(range(mine[0], mine[0] + len(mine))), case
             assert len(slots) == sum((out_hi(lib, shared, KT, n_sk, w) for w in range(n_sk))), case
 
 
@@ -89,3 +97,18 @@ def test_plans_the_kernels_cannot_run_are_refused(lib, plan, T, KT, ok):
         for w in range(plan[3]):
             lib.hvdh_tiled_run(plan[2], KT, plan[3], w, out)
             assert out[1] - out[0] < KT
+
+
+@pytest.mark.parametrize("rows", [144, 192, 256])
+@pytest.mark.parametrize("N, K", [(4096, 4096), (4096, 14336), (5120, 27648), (4096, 4128)])
+def test_small_scratch_still_splits_narrow_gemms(lib, rows, N, K):
+    """8 MiB of partial tiles (the static scratch) hold a two-way split of any
+    256 x 4096 product: one slot per worker, whether or not the split divides K."""
+    out = (ctypes.c_int32 * 4)()
+    lib.hvdh_tiled_plan(rows // 16, N, K // 32, 0, 256, ctypes.c_int64(8 << 20), out)
+    tile, n_wg, shared, n_sk = out
+    T = -(-rows // BM[tile]) * (N // BN[tile])
+    if T * 2 * BM[tile] * BN[tile] * 4 <= 8 << 20:
+        assert shared == T and n_sk >= 2 * T, (tile, n_wg, shared, n_sk)
+    else:
+        assert n_wg >= 40, (tile, n_wg, shared, n_sk)
