@@ -47,13 +47,8 @@ int prefill_rows(const hvd_config& c) { return std::min(kPrefillRows, (c.max_pos
 // prefill chunks of the 8B shape)
 constexpr int kSkinnyMaxMT = 8;
 constexpr int kMlpSingleMaxLayers = 32;      // deepest model whose verify gate/up GEMM runs single-pass by default
-constexpr int kMidMinMT = 3, kMidMaxMT = 8;  // row tiles gemm_mid takes, at least and per row block
-constexpr int kMidMinDim = 4096;                // GEMMs of fewer columns or a shorter K do not use it
 constexpr int kGemmMinBlocks = 192;          // GEMM workgroups below which the shape changes
-constexpr int kGemmSplitTarget = 256;        // workgroups a K split aims for (one per CU)
-constexpr int kGemmLongK = 256;              // K steps above which a K split pays for its reduction
 constexpr size_t kGemmPartBytes = 128u << 20;  // split-K partial tiles of one GEMM launch
-constexpr int kGemmCounters = 16384;          // split-K arrival counters (output blocks of one launch)
 constexpr int kFlowCounterWords = 1 << 17;    // one-launch step: error word and per-layer counters
 constexpr int kAoCounterBase = 64;             // attention + O launches: their counters after the error word
 constexpr int kFlowAttnItems = 128;           // attention items the one-launch step aims for
@@ -1348,39 +1343,14 @@ hvd_status forward(hvd_kv_s* k, const std::vector<SeqMeta>& seqs, std::vector<Ro
     const bool single = lm_head &&
                         ((epi == EPI_SILU && k->mlp_single_gu) || (family == PF_DOWN && k->mlp_single_down) ||
                          (k->lm_single && epi == EPI_LM));
-    // Three row tiles or more: gemm_mid, whose waves share the activations.
-    // Measured per verify step against gemm_skinny (context 2048), 8 layers of
-    // the 8B shape: 34 rows 1343 -> 1257 us, 51 1533 -> 1423, 65 1721 -> 1563,
-    // 96 2009 -> 1665, 128 2239 -> 1866; 4 layers of the 32B widths: 41 rows
-    // 1605 -> 1296 us, 128 2767 -> 1842.  At two row tiles it is no faster (8B,
-    // 17 rows: 3.95 against 3.94 ms).  Small shapes leave a workgroup a short K range
-    // or many splits, and its fixed cost decides: all GEMMs of width 2048 through
-    // gemm_mid 650 -> 642 us at 41 rows, 711 -> 718 at 64 and 836 -> 967 at 128
-    // (8 layers), of width 512 380 -> 392, 411 -> 415 and 427 -> 554.
-    if (MT >= kMidMinMT && K >= kMidMinDim && N >= kMidMinDim) {
-      const int mb = (MT + kMidMaxMT - 1) / kMidMaxMT, mtb = (MT + mb - 1) / mb;
-      // 128 columns per workgroup where those fill the CUs, and for long K (fewer
-      // activation bytes per weight byte); else 64, whose K splits have half
-      // the partial tile to publish and sum (72 rows of the 8B shape: O with
-      // 64 columns and 4 splits against 128 and 8 2.6 us per layer less, QKV
-      // with 64 and 2 against 128 and 5 2.7 us less; down with 64 and 4 against
-      // 128 and 8 0.6 us more).  No split that needs a second round of the CUs.
-      const bool can8 = a.NT % 8 == 0 && (k->ns8_mt3 || mtb > 4);
-      const int u4 = a.NT / 4 * mb, u8 = a.NT / 8 * mb;
-      auto filled = [&](int u) { return u * std::max(1, kGemmSplitTarget / u); };
-      int strips = can8 && (u8 >= k->gemm_min_blocks || a.KT >= kGemmLongK || 4 * filled(u4) < 3 * filled(u8)) ? 8 : 4;
-      const int* force = k->gemm_force[family];
-      if (force[0]) strips = force[0] >= 8 && a.NT % 8 == 0 ? 8 : 4;
-      const int units = a.NT / strips * mb;
-      int splits = std::max(1, std::min({force[0] ? force[1] : kGemmSplitTarget / units, a.KT / 8, 16}));
-      while (splits > 1 && (size_t)units * splits * mtb * 16 * strips * 16 * 4 > sx.gemm_part_bytes) --splits;
-      if (units > kGemmCounters) splits = 1;
+    if (mid_takes(MT, N, K)) {
+      const MidPlan plan = mid_plan(MT, a.NT, a.KT, k->gemm_min_blocks, k->ns8_mt3, sx.gemm_part_bytes, k->gemm_force[family]);
       if (epi == EPI_LM) {
-        lm_parts = a.NT / strips;
+        lm_parts = a.NT / plan.strips;
         a.n_part = lm_parts;
       }
       ProfScope ps(k, family, (double)N * K * 2.0);
-      HIP_TRY(launch_gemm_mid(epi, a, strips, splits, mb, mtb, !single, s));
+      HIP_TRY(launch_gemm_mid(epi, a, plan, !single, s));
       return HVD_OK;
     }
     // five row tiles (65-80 rows): one block, so the weights are read once --

@@ -523,9 +523,8 @@ static hipError_t launch_mid_mt(const GemmArgs& a, int mt, int splits, int mbloc
   return hipErrorInvalidValue;
 }
 
-// strips: 8 (128 columns per workgroup) or 4 (64)
-hipError_t launch_gemm_mid(int epi, const GemmArgs& a, int strips, int splits, int mblocks, int mt_block, bool hi_lo,
-                           hipStream_t s) {
+hipError_t launch_gemm_mid(int epi, const GemmArgs& a, const MidPlan& p, bool hi_lo, hipStream_t s) {
+  const int strips = p.strips, splits = p.splits, mblocks = p.mblocks, mt_block = p.mt_block;
   // what the kernel assumes: whole column blocks, K slots for every split,
   // partial offsets of one block within 32 bits
   if ((strips != 4 && strips != 8) || a.NT % strips || splits < 1 || mblocks < 1 || mblocks * mt_block < a.MTtot ||

@@ -7,6 +7,7 @@
 
 #include "host_state.h"
 #include "attn_order.h"
+#include "mid_plan.h"
 #include "tiled_plan.h"
 
 using hvd::HostState;
@@ -60,6 +61,17 @@ int32_t hvdh_pages(void* h, int32_t id, int32_t* out, int32_t cap) {
 }
 const char* hvdh_error(void* h) { return ((HostState*)h)->error().c_str(); }
 
+// Whether gemm_mid takes a GEMM, and its plan: strips, splits, row blocks, row tiles per block
+int hvdh_mid_plan(int32_t mtiles, int32_t N, int32_t K, int32_t wide, int64_t part_bytes, int32_t f_strips,
+                  int32_t f_splits, int32_t* out4) {
+  const int force[2] = {f_strips, f_splits};
+  const hvd::MidPlan p = hvd::mid_plan(mtiles, N / 16, K / 32, 192, wide != 0, (size_t)part_bytes, force);
+  out4[0] = p.strips;
+  out4[1] = p.splits;
+  out4[2] = p.mblocks;
+  out4[3] = p.mt_block;
+  return hvd::mid_takes(mtiles, N, K);
+}
 // Work plan of a large-batch GEMM: tile, workgroups, shared tiles, sharing workgroups
 void hvdh_tiled_plan(int32_t mtiles, int32_t N, int32_t KT, int32_t single, int32_t cus, int64_t part_bytes, int32_t* out4) {
   const hvd::TiledPlan p = hvd::tiled_plan(mtiles, N, KT, single != 0, cus, (size_t)part_bytes);

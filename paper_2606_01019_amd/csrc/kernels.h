@@ -5,6 +5,7 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "mid_plan.h"
 #include "tiled_plan.h"
 
 namespace hvd {
@@ -314,12 +315,11 @@ hipError_t launch_embed(const EmbedArgs& a, hipStream_t s);
 // ns: 16-column strips per workgroup (1, 2, 4; >= 2 for EPI_SILU); grid.x = NT / ns.
 // splits > 1 splits K across workgroups; the last split of each output block
 // to finish reduces (a.part, a.cnt).
-// hi_lo false: the hi activation part alone (honoured for the residual and
-// SiLU GEMMs at 3-4 row tiles; other shapes keep the pair)
-hipError_t launch_gemm_mid(int epi, const GemmArgs& a, int strips, int splits, int mblocks, int mt_block, bool hi_lo,
-                           hipStream_t s);
+// hi_lo false: the hi activation part alone (all but EPI_QKV).
 hipError_t launch_gemm(int epi, const GemmArgs& a, int ns, int splits, int mblocks, int mt_block, bool hi_lo,
                        hipStream_t s);
+// GEMM of 33 to 128 rows (gemm_mid.hip), or of several such row blocks; hi_lo as above.
+hipError_t launch_gemm_mid(int epi, const GemmArgs& a, const MidPlan& p, bool hi_lo, hipStream_t s);
 // Large-batch GEMM (gemm_tiled.hip): tile 0 = 128 x 128, 1 = 128 x 256,
 // 2 = 256 x 256 (8 waves), 3 = 256 x 256 (4 waves), 4 = 128 x 256 (8 waves)
 // (rows x columns), work dealt out by the plan; hi_lo false = the hi
