@@ -29,8 +29,11 @@ struct MidPlan {
 // or many splits, and its fixed cost decides: all GEMMs of width 2048 through
 // gemm_mid 650 -> 642 us at 41 rows, 711 -> 718 at 64 and 836 -> 967 at 128
 // (8 layers), of width 512 380 -> 392, 411 -> 415 and 427 -> 554.
+// Its activation offsets are 32-bit: operands of 2 GiB or more (75000 rows of K
+// 14336, where N is no multiple of 128 and the tiled kernel cannot run) stay
+// with gemm_skinny.
 inline bool mid_takes(int mtiles, int N, int K) {
-  return mtiles >= kMidMinMT && K >= kMidMinDim && N >= kMidMinDim;
+  return mtiles >= kMidMinMT && K >= kMidMinDim && N >= kMidMinDim && (int64_t)mtiles * (K / 32) * 1024 <= INT32_MAX;
 }
 
 // 128 columns per workgroup where those fill the CUs, and for long K (fewer

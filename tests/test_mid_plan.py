@@ -57,3 +57,11 @@ def test_small_scratch_does_not_halve_the_workgroups(lib, mtiles):
     if mtiles == 8:
         assert plan(lib, 8, 4096, 14336, 8 * MB)[1] == (4, 4, 1, 8)
     assert plan(lib, mtiles, 4096, 14336, 128 * MB)[1][:2] == (8, 8)
+
+
+def test_operands_past_32_bit_offsets_are_left_to_the_general_kernel(lib):
+    """launch_gemm_mid refuses them, so the dispatch must not send them there."""
+    K = 14336
+    most = (2 ** 31 - 1) // (K // 32 * 1024)
+    assert plan(lib, most, 4160, K, 128 * MB)[0]
+    assert not plan(lib, most + 1, 4160, K, 128 * MB)[0]
