@@ -778,7 +778,9 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
   // 77 -> 57.  64-row items (two per CU) and the one row group of a single
   // sequence, both of nearly equal length, keep the unit order (33-row tree at
   // context 2048 4.38 against 4.49 ms, 65 rows at 16384 6.44 against 6.52), as do the
-  // device-wide launches of flow.hip and attn_o.hip.
+  // device-wide launches of flow.hip and attn_o.hip; in it too the row groups of a
+  // chunk go to one XCD (17 rows at context 16384 28.4 us per layer against 29.1
+  // without, four 25-row drafts 92 against 98).
   // Partial slots and merge entries follow the units in either case.
   AttnItem none{};
   none.k = -1;
@@ -806,6 +808,7 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
         pieces.push_back({stream, (int)i, ci, std::min(units[i].keys, (ci + 1) * chunk) - ci * chunk});
     }
     if (by_length && (members.size() > 1 || units.size() > (size_t)c.n_kv_heads)) pieces = attn_order(pieces);
+    else pieces = attn_interleave(pieces);
     for (const AttnPiece& q : pieces) {
       const int nch = q.unit < 0 ? 0 : nch_u[q.unit];
       p.items.push_back(nch == 0   ? none

@@ -16,6 +16,36 @@ struct AttnPiece {
   int stream, unit, chunk, keys;
 };
 
+// The pieces in unit order, but for streams of several units (row groups that read
+// the same chunks): there the units' pieces of one chunk go kXcds positions apart,
+// next to each other in dispatch order -- the same XCD at nearly the same time,
+// so that a chunk comes from HBM once and from that XCD's L2 for the others.
+// Chunks in runs of kXcds: run position j of unit r at run base + kXcds r + j, a
+// no-op piece (unit -1) where a unit has fewer chunks.  Pieces in unit order.
+inline std::vector<AttnPiece> attn_interleave(const std::vector<AttnPiece>& in) {
+  std::vector<AttnPiece> out;
+  out.reserve(in.size() + in.size() / 4);
+  std::vector<size_t> unit;  // first piece of each unit of the stream, and the end
+  for (size_t i0 = 0, i1; i0 < in.size(); i0 = i1) {
+    unit.clear();
+    for (i1 = i0; i1 < in.size() && in[i1].stream == in[i0].stream; ++i1)
+      if (i1 == i0 || in[i1].unit != in[i1 - 1].unit) unit.push_back(i1);
+    unit.push_back(i1);
+    const size_t n = unit.size() - 1;
+    if (n == 1) {
+      out.insert(out.end(), in.begin() + i0, in.begin() + i1);
+      continue;
+    }
+    size_t most = 0;
+    for (size_t r = 0; r < n; ++r) most = std::max(most, unit[r + 1] - unit[r]);
+    for (size_t c0 = 0; c0 < most; c0 += kXcds)
+      for (size_t r = 0; r < n; ++r)
+        for (size_t c = c0; c < std::min(most, c0 + kXcds); ++c)
+          out.push_back(c < unit[r + 1] - unit[r] ? in[unit[r] + c] : AttnPiece{-1, -1, 0, 0});
+  }
+  return out;
+}
+
 // The items as kXcds interleaved queues: workgroup i runs on XCD i % kXcds
 // (round-robin dispatch), so position i belongs to queue i % kXcds.  The items
 // of one (stream, chunk) read the same keys and go to one queue; these bundles

@@ -95,12 +95,12 @@ void hvdh_tiled_run(int32_t n_shared, int32_t KT, int32_t n_sk, int32_t w, int32
 int32_t hvdh_tiled_slot(int32_t n_shared, int32_t KT, int32_t n_sk, int32_t w, int32_t t) {
   return hvd::SharedRuns(n_shared, KT, n_sk).slot0(w) + t;
 }
-// Launch order of attention items [n][4] (stream, unit, chunk, keys); returns the
-// count, no-op pieces (unit -1) included
-int32_t hvdh_attn_order(int32_t n, const int32_t* in, int32_t* out, int32_t cap) {
+// Launch order of attention items [n][4] (stream, unit, chunk, keys), longest first or
+// interleaved; returns the count, no-op pieces (unit -1) included
+static int32_t attn_pieces(bool longest_first, int32_t n, const int32_t* in, int32_t* out, int32_t cap) {
   std::vector<hvd::AttnPiece> p(n);
   for (int32_t i = 0; i < n; ++i) p[i] = {in[4 * i], in[4 * i + 1], in[4 * i + 2], in[4 * i + 3]};
-  p = hvd::attn_order(p);
+  p = longest_first ? hvd::attn_order(p) : hvd::attn_interleave(p);
   for (size_t i = 0; i < p.size() && (int32_t)i < cap; ++i) {
     out[4 * i] = p[i].stream;
     out[4 * i + 1] = p[i].unit;
@@ -108,5 +108,11 @@ int32_t hvdh_attn_order(int32_t n, const int32_t* in, int32_t* out, int32_t cap)
     out[4 * i + 3] = p[i].keys;
   }
   return (int32_t)p.size();
+}
+int32_t hvdh_attn_order(int32_t n, const int32_t* in, int32_t* out, int32_t cap) {
+  return attn_pieces(true, n, in, out, cap);
+}
+int32_t hvdh_attn_interleave(int32_t n, const int32_t* in, int32_t* out, int32_t cap) {
+  return attn_pieces(false, n, in, out, cap);
 }
 }

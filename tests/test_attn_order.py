@@ -22,10 +22,10 @@ def lib():
     return ctypes.CDLL(path)
 
 
-def order(lib, pieces):
+def order(lib, pieces, how="order"):
     a = np.ascontiguousarray(pieces, np.int32)
     out = np.zeros((2 * len(a) + 8, 4), np.int32)
-    n = lib.hvdh_attn_order(len(a), a.ctypes.data_as(ctypes.c_void_p), out.ctypes.data_as(ctypes.c_void_p), len(out))
+    n = getattr(lib, "hvdh_attn_" + how)(len(a), a.ctypes.data_as(ctypes.c_void_p), out.ctypes.data_as(ctypes.c_void_p), len(out))
     assert n <= 2 * len(a)
     return out[:n]
 
@@ -71,3 +71,27 @@ def test_order(lib, name):
         for x, q in enumerate(queues):
             for s, _, c, _ in q:
                 assert home.setdefault((s, c), x) == x
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_interleave(lib, name):
+    """Unit order: every item once, and the row groups that read a chunk of one
+    stream on one XCD (positions 8 apart), next to each other."""
+    pieces = pieces_of(*CASES[name])
+    out = [tuple(int(v) for v in r) for r in order(lib, pieces, "interleave")]
+    real = [p for p in out if p[1] >= 0]
+    assert sorted(real) == sorted(pieces) and len(out) <= 2 * len(pieces)
+    assert [p[0] for p in real] == sorted(p[0] for p in real)  # stream after stream
+    groups, at = {}, {}
+    for i, (s, u, c, _) in enumerate(out):
+        if u >= 0:
+            groups.setdefault(s, set()).add(u)
+            at.setdefault((s, c), []).append((u, i))
+    most = {s: 1 + max(c for r, c in at if r == s) for s in groups}
+    for (s, c), members in at.items():
+        members.sort()
+        assert members[-1][1] - members[0][1] <= 8 * (len(groups[s]) - 1)
+        if c // 8 < most[s] // 8:  # (a stream's last run may be shorter)
+            assert len({i % 8 for _, i in members}) == 1
+    if all(len(g) == 1 for g in groups.values()):
+        assert out == pieces  # one row group each: the order is the units'
