@@ -730,6 +730,7 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
   };
   std::vector<Unit> units;
   int64_t total_keys = 0;
+  int most_keys = 0, least_keys = 1 << 30;
   for (int b : members) {
     const SeqMeta& s = seqs[b];
     const int R = (s.k + 1) * G;
@@ -740,6 +741,8 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
         const int keys = s.ctx + i_max + 1;
         units.push_back({b, g, rg, keys});
         total_keys += keys;
+        most_keys = std::max(most_keys, keys);
+        least_keys = std::min(least_keys, keys);
       }
   }
   // chunk: a power-of-two number of positions, the largest that still gives
@@ -768,60 +771,59 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
     chunk = 32;
     while (chunk < (1 << 20) && n_items_at(chunk) > max_items) chunk *= 2;
   }
-  // Order of the items (attn_order.h): eight interleaved queues, one per XCD, the
-  // longest items first.  The row groups of one (sequence, kv head) that read a
-  // chunk share a queue, hence an XCD: the chunk comes from HBM once and from
-  // that XCD's L2 for the others.  In unit order the last workgroups of a
-  // launch were as long as any, and half of the CUs waited for them: attention
-  // of a 2048-token prefill chunk 180 -> 147 us per layer, of the 848-row batch's
-  // 256-row items 143 -> 109, 384-row items of the 32B widths at context 8192
-  // 77 -> 57.  64-row items (two per CU) and the one row group of a single
-  // sequence, both of nearly equal length, keep the unit order (33-row tree at
-  // context 2048 4.38 against 4.49 ms, 65 rows at 16384 6.44 against 6.52), as do the
-  // device-wide launches of flow.hip and attn_o.hip; in it too the row groups of a
-  // chunk go to one XCD (17 rows at context 16384 28.4 us per layer against 29.1
-  // without, four 25-row drafts 92 against 98).
-  // Partial slots and merge entries follow the units in either case.
-  AttnItem none{};
-  none.k = -1;
-  std::vector<int> nch_u, slot_u;
+  // the chunk is lengthened until the partials fit
+  std::vector<int> slot_u(units.size());
   for (;;) {
-    p.items.clear();
-    p.heads.clear();
-    nch_u.assign(units.size(), 0);
-    slot_u.assign(units.size(), -1);
-    int slots = 0;
+    size_t slots = 0;
     for (size_t i = 0; i < units.size(); ++i) {
-      const Unit& u = units[i];
-      const int nch = (u.keys + chunk - 1) / chunk;
-      nch_u[i] = nch;
-      if (nch > 1) {
-        slot_u[i] = slots;
-        p.heads.push_back(item(u, 0, nch, slots, chunk));
-        slots += nch;
-      }
+      const int nch = (units[i].keys + chunk - 1) / chunk;
+      slot_u[i] = nch > 1 ? (int)slots : -1;
+      if (nch > 1) slots += nch;
     }
-    std::vector<AttnPiece> pieces;
-    for (size_t i = 0; i < units.size(); ++i) {
-      const int stream = units[i].b * c.n_kv_heads + units[i].g;
-      for (int ci = 0; ci < nch_u[i]; ++ci)
-        pieces.push_back({stream, (int)i, ci, std::min(units[i].keys, (ci + 1) * chunk) - ci * chunk});
-    }
-    if (by_length && (members.size() > 1 || units.size() > (size_t)c.n_kv_heads)) pieces = attn_order(pieces);
-    else pieces = attn_interleave(pieces);
-    for (const AttnPiece& q : pieces) {
-      const int nch = q.unit < 0 ? 0 : nch_u[q.unit];
-      p.items.push_back(nch == 0   ? none
-                        : nch == 1 ? item(units[q.unit], 0, 1, -1, chunk)
-                                   : item(units[q.unit], q.chunk, nch, slot_u[q.unit] + q.chunk, chunk));
-    }
-    if ((size_t)slots * rpi <= part_rows_free) {  // partial buffer rows
-      p.part_rows = (size_t)slots * rpi;
+    if (slots * rpi <= part_rows_free) {  // partial buffer rows
+      p.part_rows = slots * rpi;
       break;
     }
     if (chunk >= (1 << 20)) return false;
     // longer chunks: multiples of kAttnChunk above it (looped in LDS-sized pieces)
     chunk = chunk < kAttnChunk ? std::min(kAttnChunk, chunk * 2) : chunk * 2;
+  }
+  auto nch_of = [&](int i) { return (units[i].keys + chunk - 1) / chunk; };
+  p.items.clear();
+  p.heads.clear();
+  std::vector<AttnPiece> pieces;
+  for (size_t i = 0; i < units.size(); ++i) {
+    const int stream = units[i].b * c.n_kv_heads + units[i].g, nch = nch_of((int)i);
+    if (nch > 1) p.heads.push_back(item(units[i], 0, nch, slot_u[i], chunk));
+    for (int ci = 0; ci < nch; ++ci)
+      pieces.push_back({stream, (int)i, ci, std::min(units[i].keys, (ci + 1) * chunk) - ci * chunk});
+  }
+  // Order of the items (attn_order.h).  Items of 128 rows or more run one per CU:
+  // as eight queues, one per XCD, the longest first, where that shortens the end
+  // of the launch -- several sequences with more items than CUs, or row groups
+  // of one sequence (prefill) whose key counts differ by a chunk.  In unit order
+  // the last workgroups are as long as any, and half of the CUs wait for them:
+  // attention of a 2048-token prefill chunk 180 -> 145 us per layer, of a 300-token
+  // one 20 -> 13, of the 848-row batch's 256-row items 143 -> 109, of two 65-row
+  // drafts at context 16384 122 -> 82, 384-row items of the 32B widths at context
+  // 8192 77 -> 57.  One round of items or items of equal length gain nothing from it
+  // and pay for the sort (two 64-row drafts of a model of width 1024: 11.8 us in
+  // unit order, 12.4 by length, and the step 692 against 717 us).
+  // Otherwise, for 64-row items (two per CU) and for the device-wide launches of
+  // flow.hip and attn_o.hip: unit order, the row groups of a chunk on one XCD
+  // (17 rows at context 16384 28.4 us per layer against 29.1 without, four
+  // 25-row drafts 92 against 98).
+  // Partial slots and merge entries follow the units in either case.
+  const bool longest_first = by_length && (members.size() > 1 ? pieces.size() > (size_t)kCUs : most_keys - least_keys >= chunk);
+  pieces = longest_first ? attn_order(pieces) : attn_interleave(pieces);
+  AttnItem none{};
+  none.k = -1;
+  p.items.reserve(pieces.size());
+  for (const AttnPiece& q : pieces) {
+    const int nch = q.unit < 0 ? 0 : nch_of(q.unit);
+    p.items.push_back(nch == 0   ? none
+                      : nch == 1 ? item(units[q.unit], 0, 1, -1, chunk)
+                                 : item(units[q.unit], q.chunk, nch, slot_u[q.unit] + q.chunk, chunk));
   }
   p.chunk = chunk;
   p.rpi = rpi;

@@ -95,3 +95,45 @@ def test_interleave(lib, name):
             assert len({i % 8 for _, i in members}) == 1
     if all(len(g) == 1 for g in groups.values()):
         assert out == pieces  # one row group each: the order is the units'
+
+
+
+def model_order(pieces):
+    """attn_order by comparison sorts."""
+    pieces = sorted(pieces, key=lambda p: (p[0], p[2], p[1]))
+
+    def deal(bundles):
+        load, queues = [0] * 8, [[] for _ in range(8)]
+        for b in sorted(bundles, key=lambda b: -sum(p[3] for p in b)):
+            x = load.index(min(load))
+            load[x] += sum(p[3] for p in b)
+            queues[x] += b
+        return queues, max(load) * 8 <= sum(load) + sum(load) // 8
+
+    bundles = {}
+    for p in pieces:
+        bundles.setdefault((p[0], p[2]), []).append(p)
+    queues, even = deal(list(bundles.values()))
+    if not even:
+        queues, _ = deal([[p] for p in pieces])
+    by_length = lambda ps: sorted(ps, key=lambda p: (-p[3], p[0], p[2], p[1]))
+    queues = [by_length(q) for q in queues]
+    longest = max(len(q) for q in queues)
+    if longest * 8 > 2 * len(pieces):
+        return by_length(pieces)
+    out = [q[i] if i < len(q) else (-1, -1, 0, 0) for i in range(longest) for q in queues]
+    while out[-1][1] < 0:
+        out.pop()
+    return out
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_order_equals_the_model(lib, seed):
+    r = np.random.default_rng(seed)
+    chunk, heads = int(r.choice([32, 64, 256, 1024])), int(r.choice([1, 2, 3, 8]))
+    seqs = []
+    for _ in range(int(r.integers(1, 9))):
+        first, groups = int(r.choice([r.integers(1, 90), r.integers(90, 9000)])), int(r.choice([1, 1, 2, 3, 32]))
+        seqs.append([first + 64 * i for i in range(groups)])
+    pieces = pieces_of(seqs, heads, chunk)
+    assert [tuple(int(v) for v in p) for p in order(lib, pieces)] == model_order(pieces)
