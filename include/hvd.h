@@ -126,7 +126,8 @@ hvd_status hvd_prefill(hvd_model m, hvd_kv kv, int32_t seq_id, const int32_t* to
  * the target's argmax after the accepted prefix (lowest id on ties).  The
  * committed block is draft[0:a_b] followed by next_token[b].
  * logits (nullable, DEVICE pointer) receives fp32 logits [sum(k_b+1)][vocab],
- * rows packed by sequence -- for parity checks only (extra HBM writes).
+ * rows packed by sequence -- for parity checks only (extra HBM writes); any
+ * 4-byte aligned address.
  * K/V of all k_b + 1 rows is written tentatively; hvd_commit decides how many
  * stay.  A second verify of a sequence before its commit is HVD_ERR_STATE. */
 hvd_status hvd_verify(hvd_model m, hvd_kv kv, int32_t batch, const int32_t* seq_ids,

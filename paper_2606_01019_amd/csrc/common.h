@@ -112,6 +112,16 @@ __device__ __forceinline__ uint32_t pack_h2(float lo, float hi) {
   return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)lo) | ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)hi) << 16);
 }
 
+// Eight logits of one row, 16 bytes per store.  Callers may pass any 4-byte
+// aligned buffer, and that is all global stores of several dwords need; the type
+// says so, so that the compiler does not take more for granted.  (A branch to
+// 4-byte stores instead cost the LM head of 853 rows 960 -> 1056 us.)
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void store_logits8(float* p, const float (&v)[8]) {
+  ((f32x4_a4*)p)[0] = f32x4_a4{v[0], v[1], v[2], v[3]};
+  ((f32x4_a4*)p)[1] = f32x4_a4{v[4], v[5], v[6], v[7]};
+}
+
 // Synchronisation points of work done inside a larger kernel (the one-launch
 // verify step): wait() runs once the work's first constant inputs (weights,
 // cached K/V) are requested and before any input another workgroup of the

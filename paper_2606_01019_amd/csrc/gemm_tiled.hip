@@ -296,11 +296,7 @@ __device__ __forceinline__ void epi_block(const GemmArgs& a, const f32x16& c0, c
         }
       }
       if (R < a.M) {
-        if (a.logits) {
-          float4* lp = (float4*)(a.logits + (size_t)R * a.vocab + C);
-          lp[0] = float4{v[0], v[1], v[2], v[3]};
-          lp[1] = float4{v[4], v[5], v[6], v[7]};
-        }
+        if (a.logits) store_logits8(a.logits + (size_t)R * a.vocab + C, v);
         if (o == 0) {
           a.part_val[(size_t)R * a.n_part + (col0 >> 6)] = best;
           a.part_idx[(size_t)R * a.n_part + (col0 >> 6)] = bidx;
