@@ -300,7 +300,8 @@ hvd_status hvd_profile_read(hvd_kv kv, int32_t family, double* ms, int64_t* laun
  *   sub-chunk stages (power of two, 2..16).  HVD_OPT_SKINNY_MAX_MT (8): row
  *   tiles above which GEMMs take the MFMA-tiled kernel.  HVD_OPT_NS8_MT3 (1):
  *   8-strip GEMM blocks at three and four row tiles.
- *   HVD_OPT_PREFILL_ROWS (0 = policy): prefill chunk rows, a multiple of 16.
+ *   HVD_OPT_PREFILL_ROWS (0 = policy): prefill chunk rows at most, a multiple
+ *   of 16 up to 2048 (or max_seqs * (max_draft + 1), if that is more).
  * HVD_OPT_GEMM_SHAPE + f, f = 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head:
  *   skinny GEMM shape of that GEMM, strips * 100 + K splits (0 = policy).
  * HVD_OPT_TILED_SHAPE + f: tiled GEMM shape, (tile + 1) * 100 + K splits

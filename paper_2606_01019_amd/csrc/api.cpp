@@ -2107,7 +2107,8 @@ extern "C" hvd_status hvd_kv_set_option(hvd_kv k, int32_t option, int32_t value)
       } else if (option == HVD_OPT_NS8_MT3) {
         k->ns8_mt3 = value != 0;
       } else {
-        if (value != 0 && (value < 16 || value % 16 || value > k->max_rows))
+        // (a chunk never has more rows than the prompt, hence than a short rotary table)
+        if (value != 0 && (value < 16 || value % 16 || value > std::max(k->max_rows, kPrefillRows)))
           return set_err(HVD_ERR_ARG, "HVD_OPT_PREFILL_ROWS must be 0 or a multiple of 16 within the row workspace");
         k->prefill_rows = value;
       }

@@ -54,3 +54,32 @@ def test_prefill_then_verify(model, n):
         at += len(d) + 1
     print(rep)
     kv.close()
+
+
+def test_chunk_rows_above_a_short_rotary_table():
+    """HVD_OPT_PREFILL_ROWS may exceed max_pos: a chunk has at most the prompt's
+    rows.  512-row chunks of a 95-token prompt leave what one 96-row chunk leaves."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2606_01019_amd as hvd
+    short = ModelConfig("short", 2, 256, 4, 4, 64, 1024, 4096, 1.0e4, max_pos=100, max_draft=4)
+    gm = hvd.Model(short, make_weights(short, seed=29, gain_std=0.1))
+    kv = hvd.KVCache(gm, max_seqs=1, n_pages=8)
+    prompt = wt.uniform_context(wt.rng_for("context", 301), 95, short.vocab)
+    out = []
+    for rows in (0, 16, 128, 512, 2048):
+        kv.set_option(hvd.hvd.HVD_OPT_PREFILL_ROWS, rows)
+        print(f"chunks of {rows} rows", flush=True)
+        kv.prefill(0, prompt)
+        lg = torch.empty((5, short.vocab), dtype=torch.float32, device="cuda")
+        kv.verify([0], [94], [np.asarray([1, 2, 3, 4])], logits=lg)
+        out.append(lg.cpu())
+        kv.seq_free(0)
+    for lg in out:
+        assert float((lg - out[0]).abs().max()) <= 2e-3
+    for bad in (-16, 8, 24, 4096):
+        with pytest.raises(hvd.HvdError):
+            kv.set_option(hvd.hvd.HVD_OPT_PREFILL_ROWS, bad)
+    kv.close()
+    gm.close()
