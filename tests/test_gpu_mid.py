@@ -3,7 +3,7 @@ paths the tiny decoder does not: 8 q / 2 kv heads of 128 (group 4), rotary
 theta 5e5, weight-streaming GEMMs with 2 and 4 strips per workgroup, the
 pipelined K loop with its tail, the K split with its finish pass (down
 projection, K = 8192), split-KV attention with the combine pass, prefill
-in 512-row chunks with a ragged tail, 1 to 5 row tiles per verify
+in a 512-row chunk and a ragged one, 1 to 5 row tiles per verify
 (k = 0 .. 64), and the largest batch a 32-sequence handle takes."""
 
 import numpy as np
@@ -42,6 +42,7 @@ def test_mid_verify_matches_oracle(mid, k):
     kv = hvd.KVCache(gm, max_seqs=1, n_pages=128)
     ctx = wt.uniform_context(wt.rng_for("context", 40 + k), 600, MID.vocab)
     st = oracle.prefill(om, ctx)
+    kv.set_option(hvd.hvd.HVD_OPT_PREFILL_ROWS, 512)
     kv.prefill(0, ctx)
     drng = wt.rng_for("draft", 40 + k)
     g, _ = oracle.greedy_decode(om, st, min(k, 12) + 1)

@@ -1,8 +1,8 @@
 """GPU parity of every MFMA-tiled GEMM variant, whatever the launch policy
 would pick: each of the five tile shapes (128x128, 128x256 with four waves
 of 64x128 or eight of 64x64, 256x256 with eight waves of 64x128 or four of
-128x128), without a K split and with a two-way split summed inside the
-launch, forced for all five GEMM families at once.
+128x128), without a K split and with a two-way split summed by a
+second kernel, forced for all five GEMM families at once.
 
 The decoder has one layer of model width 2048, so the attention projections
 have enough K steps for a split too: 16 q / 4 kv heads of 128, SwiGLU 4096,
