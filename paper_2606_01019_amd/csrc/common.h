@@ -112,6 +112,21 @@ __device__ __forceinline__ uint32_t pack_h2(float lo, float hi) {
   return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)lo) | ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)hi) << 16);
 }
 
+// Eight values as the fp16 hi + lo pair, 16 bytes each.
+__device__ __forceinline__ void split8(const float (&v)[8], uint4& hi, uint4& lo) {
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint16_t h0, l0, h1, l1;
+    split_f16(v[2 * i], h0, l0);
+    split_f16(v[2 * i + 1], h1, l1);
+    h[i] = h0 | ((uint32_t)h1 << 16);
+    l[i] = l0 | ((uint32_t)l1 << 16);
+  }
+  hi = uint4{h[0], h[1], h[2], h[3]};
+  lo = uint4{l[0], l[1], l[2], l[3]};
+}
+
 // Eight logits of one row, 16 bytes per store.  Callers may pass any 4-byte
 // aligned buffer, and that is all global stores of several dwords need; the type
 // says so, so that the compiler does not take more for granted.  (A branch to
@@ -139,6 +154,23 @@ struct NoHooks {
 // operations are outstanding (lgkmcnt and expcnt left alone): vmcnt is
 // split over bits 3:0 and 15:14.
 __host__ __device__ constexpr int vmcnt_enc(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Waits until at most N of this wave's vector-memory operations are in flight.
+template <int N>
+__device__ __forceinline__ void vm_wait() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt(vmcnt_enc(N));
+}
+// Workgroup barrier without the memory fence of __syncthreads (whose release
+// would wait for every LDS copy in flight); the empty asm statements keep the
+// compiler from moving LDS accesses across it.
+__device__ __forceinline__ void block_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 // Across the four 16-lane rows of a wave: every lane gets the max (sum) of
 // the values at its position l % 16 in all four rows.  The row-swap

@@ -41,26 +41,11 @@
 
 namespace hvd {
 
-typedef __attribute__((address_space(3))) void lds_void;
-
 constexpr int kMidWaves = 4, kMidThreads = 64 * 2 * kMidWaves;  // streaming waves; as many copy
 
 // K steps of weights in flight per streaming wave (4 NSW registers each)
 constexpr int mid_depth(int MT, int NSW) { return NSW == 1 ? 24 : MT >= 7 ? 12 : 16; }
 constexpr int kMidSlots = 4;  // ring slots: the copies of two may be in flight
-
-template <int N>
-__device__ __forceinline__ void mid_vm_wait() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(vmcnt_enc(N));
-}
-// Workgroup barrier without a memory fence (which would wait for every load
-// in flight).
-__device__ __forceinline__ void mid_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 // Inputs of a thread's octets (residual stream and gains, or rotary factors),
 // requested before the partial tiles are published or read.
@@ -111,19 +96,6 @@ __device__ __forceinline__ void mid_epilogue(const GemmArgs& a, const float* til
     const float4 x = *(const float4*)(tile + r * P + c), y = *(const float4*)(tile + r * P + c + 4);
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
     v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
-  };
-  auto split8 = [](const float (&v)[8], uint4& hi, uint4& lo) __attribute__((always_inline)) {
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      uint16_t h0, l0, h1, l1;
-      split_f16(v[2 * i], h0, l0);
-      split_f16(v[2 * i + 1], h1, l1);
-      h[i] = h0 | ((uint32_t)h1 << 16);
-      l[i] = l0 | ((uint32_t)l1 << 16);
-    }
-    hi = uint4{h[0], h[1], h[2], h[3]};
-    lo = uint4{l[0], l[1], l[2], l[3]};
   };
   if constexpr (EPI == EPI_RESID) {
     using E = MidX<MT, COLS, EPI, NT>;
@@ -346,11 +318,11 @@ __global__ __launch_bounds__(kMidThreads, 2) void gemm_mid(GemmArgs a, int n_cb,
     if constexpr (EPI == EPI_QKV)
       if (tid - 64 * kMidWaves < ROWS) rows[tid - 64 * kMidWaves] = RowMeta{rm.x, rm.y, rm.z, rm.w};
     for (int i = 0; i < n; ++i) {
-      mid_vm_wait<(ST - 2) * MT>();
-      mid_barrier();
+      vm_wait<(ST - 2) * MT>();
+      block_barrier();
       copy(i + ST - 1);
     }
-    mid_vm_wait<0>();  // no copy may land after the ring is reused
+    vm_wait<0>();  // no copy may land after the ring is reused
   } else {
     const uint32_t wstride = (uint32_t)a.wk * 16;
     const char* wbase[NSW];
@@ -393,7 +365,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void gemm_mid(GemmArgs a, int n_cb,
     for (; k + QD < ke; k += QD) {
 #pragma unroll
       for (int q = 0; q < QD; ++q) {
-        if (q % KS == 0) mid_barrier();
+        if (q % KS == 0) block_barrier();
         step(q, q % KS);
         load_w(q, k + q + QD);
         if (q % KS == KS - 1) next_slot();
@@ -403,7 +375,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void gemm_mid(GemmArgs a, int n_cb,
 #pragma unroll
     for (int q = 0; q < QD; q += KS) {
       if (k + q >= ke) break;
-      mid_barrier();
+      block_barrier();
       if (k + q + KS <= ke) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) step(q + ks, ks);
@@ -439,7 +411,7 @@ __global__ __launch_bounds__(kMidThreads, 2) void gemm_mid(GemmArgs a, int n_cb,
       if (e < TOTAL)
         st_f4_dev(part, (uint32_t)((split * ROWS * COLS + e * 4) * 4), *(const float4*)(tile + e / QPR * P + e % QPR * 4));
     }
-    mid_vm_wait<0>();  // this thread's stores are done
+    vm_wait<0>();  // this thread's stores are done
     __syncthreads();   // (and every thread has read its part of the tile)
     int* flag = (int*)tile;
     if (tid == 0) *flag = atomicAdd(a.cnt + unit, 1u) == (uint32_t)nsplit - 1u;

@@ -33,24 +33,6 @@ namespace hvd {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-typedef __attribute__((address_space(3))) void lds_void;
-
-// s_waitcnt on the vector-memory counter only (gfx9 encoding: vmcnt in bits
-// 3:0 and 15:14, expcnt and lgkmcnt left at their maxima).
-template <int N>
-__device__ __forceinline__ void vm_wait() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-// Workgroup barrier without the memory fence of __syncthreads (whose release
-// would wait for every LDS copy in flight); the empty asm statements keep the
-// compiler from moving LDS accesses across it.
-__device__ __forceinline__ void block_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 __device__ __forceinline__ f32x16 mfma32_f16(const u32x4& a, const u32x4& b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
                                                 0, 0);
@@ -107,20 +89,6 @@ __device__ __forceinline__ void epi_load_x(const GemmArgs& a, int row0, int col0
       e.x[it][1] = xp[1];
     }
   }
-}
-
-__device__ __forceinline__ void split8(const float (&v)[8], uint4& hi, uint4& lo) {
-  uint32_t h[4], l[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    uint16_t h0, l0, h1, l1;
-    split_f16(v[2 * i], h0, l0);
-    split_f16(v[2 * i + 1], h1, l1);
-    h[i] = h0 | ((uint32_t)h1 << 16);
-    l[i] = l0 | ((uint32_t)l1 << 16);
-  }
-  hi = uint4{h[0], h[1], h[2], h[3]};
-  lo = uint4{l[0], l[1], l[2], l[3]};
 }
 
 // c0, c1: the two 32 x 32 accumulators of the block at (row0, col0); lds: the
@@ -322,7 +290,7 @@ __global__ __launch_bounds__(64 * WY * WX, tiled_occupancy(WM, WN)) void gemm_ti
   constexpr int LPT = NF / NW;  // 16-byte loads per thread per K step (NF*64 / (64*NW))
   static_assert(NF % NW == 0, "fragments per step");
   // ring depth: two workgroups per CU for the small tiles, else one
-    constexpr int LDS_BUDGET = (NW == 4 && WM * WN < 16) ? 76 * 1024 : 150 * 1024;
+  constexpr int LDS_BUDGET = (NW == 4 && WM * WN < 16) ? 76 * 1024 : 150 * 1024;
   constexpr int ST0 = LDS_BUDGET / (NF * 1024);
   constexpr int ST = ST0 < 3 ? 3 : (ST0 > 6 ? 6 : ST0);
   __shared__ u32x4 sbuf[ST][NF][64];
@@ -369,7 +337,7 @@ __global__ __launch_bounds__(64 * WY * WX, tiled_occupancy(WM, WN)) void gemm_ti
   }
   const int rb = tile % RB, cb = tile / RB;
   const int mt0 = rb * AF;
-  if (!first) __syncthreads();  // every wave has read its last operands (and the arrival flag) of the ring
+  if (!first) __syncthreads();  // every wave has read its last operands of the ring
   first = false;
 
   // this thread's share of a K step: unit u = q*64*NW + tid is fragment
