@@ -303,7 +303,11 @@ hvd_status hvd_profile_read(hvd_kv kv, int32_t family, double* ms, int64_t* laun
  *   HVD_OPT_PREFILL_ROWS (0 = policy): prefill chunk rows at most, a multiple
  *   of 16 up to 2048 (or max_seqs * (max_draft + 1), if that is more).
  * HVD_OPT_GEMM_SHAPE + f, f = 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head:
- *   skinny GEMM shape of that GEMM, strips * 100 + K splits (0 = policy).
+ *   shape of that GEMM at up to HVD_OPT_SKINNY_MAX_MT row tiles, strips * 100 +
+ *   K splits (0 = policy), strips 1, 2, 4 or 8.  From 33 rows on, GEMMs of at
+ *   least 4096 columns and K run on column blocks of 4 or 8 strips: 1 and 2 count
+ *   as 4 there, 8 as 4 where the strips are no multiple of 8, and there is at
+ *   most one K split per 256 of K.
  * HVD_OPT_TILED_SHAPE + f: tiled GEMM shape, (tile + 1) * 100 + K splits
  *   (tile 0 = 128x128, 1 = 128x256, 2 = 256x256 / 8 waves, 3 = 256x256 / 4
  *   waves, 4 = 128x256 / 8 waves; 0 = policy). */

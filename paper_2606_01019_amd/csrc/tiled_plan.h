@@ -21,8 +21,8 @@ constexpr int kTileBN[kTiles] = {128, 256, 256, 256, 256};
 
 // n_wg workgroups.  The last n_shared tiles of the grid are shared: their K
 // steps, taken as one list, are dealt to the first n_sk workgroups in equal
-// contiguous runs; the other tiles go whole to the workgroups in turn.
-// n_shared <= n_sk <= n_wg, so that a run spans at most two tiles.
+// contiguous runs (the published "stream-K" decomposition); the other tiles go whole to the workgroups in turn.
+// n_shared < n_sk <= n_wg, so that a run spans at most two tiles.
 struct TiledPlan {
   int tile = 0, n_wg = 0, n_shared = 0, n_sk = 0;
 };
