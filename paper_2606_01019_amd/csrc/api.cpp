@@ -733,7 +733,6 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
   };
   std::vector<Unit> units;
   int64_t total_keys = 0;
-  int most_keys = 0, least_keys = 1 << 30;
   for (int b : members) {
     const SeqMeta& s = seqs[b];
     const int R = (s.k + 1) * G;
@@ -744,8 +743,6 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
         const int keys = s.ctx + i_max + 1;
         units.push_back({b, g, rg, keys});
         total_keys += keys;
-        most_keys = std::max(most_keys, keys);
-        least_keys = std::min(least_keys, keys);
       }
   }
   // chunk: a power-of-two number of positions, the largest that still gives
@@ -803,21 +800,20 @@ bool plan_attention(const hvd_config& c, const HostState& hs, const std::vector<
   }
   // Order of the items (attn_order.h).  Items of 128 rows or more run one per CU:
   // as eight queues, one per XCD, the longest first, where that shortens the end
-  // of the launch -- several sequences with more items than CUs, or row groups
-  // of one sequence (prefill) whose key counts differ by a chunk.  In unit order
-  // the last workgroups are as long as any, and half of the CUs wait for them:
+  // of the launch by its estimate.  In unit order the last workgroups are as long as
+  // any, and half of the CUs wait for them:
   // attention of a 2048-token prefill chunk 180 -> 145 us per layer, of a 300-token
   // one 20 -> 13, of the 848-row batch's 256-row items 143 -> 109, of two 65-row
   // drafts at context 16384 122 -> 82, 384-row items of the 32B widths at context
-  // 8192 77 -> 57.  One round of items or items of equal length gain nothing from it
-  // and pay for the sort (two 64-row drafts of a model of width 1024: 11.8 us in
-  // unit order, 12.4 by length, and the step 692 against 717 us).
+  // 8192 77 -> 57.  128-row items (head dim 64) of one sequence are the exception: a
+  // prompt's row groups read one chunk after the other in unit order, and 16000
+  // tokens through 4 layers of width 1024 take 9.71 ms, by length 9.94.
   // Otherwise, for 64-row items (two per CU) and for the device-wide launches of
   // flow.hip and attn_o.hip: unit order, the row groups of a chunk on one XCD
   // (17 rows at context 16384 28.4 us per layer against 29.1 without, four
   // 25-row drafts 92 against 98).
   // Partial slots and merge entries follow the units in either case.
-  const bool longest_first = by_length && (members.size() > 1 ? pieces.size() > (size_t)kCUs : most_keys - least_keys >= chunk);
+  const bool longest_first = by_length && (members.size() > 1 || rpi > kAttnRows) && attn_order_pays(pieces, kCUs);
   pieces = longest_first ? attn_order(pieces) : attn_interleave(pieces);
   AttnItem none{};
   none.k = -1;

@@ -109,6 +109,12 @@ static int32_t attn_pieces(bool longest_first, int32_t n, const int32_t* in, int
   }
   return (int32_t)p.size();
 }
+// Whether the launch gains from the longest-first order
+int hvdh_attn_order_pays(int32_t n, const int32_t* in, int32_t cus) {
+  std::vector<hvd::AttnPiece> p(n);
+  for (int32_t i = 0; i < n; ++i) p[i] = {in[4 * i], in[4 * i + 1], in[4 * i + 2], in[4 * i + 3]};
+  return hvd::attn_order_pays(p, cus);
+}
 int32_t hvdh_attn_order(int32_t n, const int32_t* in, int32_t* out, int32_t cap) {
   return attn_pieces(true, n, in, out, cap);
 }

@@ -137,3 +137,19 @@ def test_order_equals_the_model(lib, seed):
         seqs.append([first + 64 * i for i in range(groups)])
     pieces = pieces_of(seqs, heads, chunk)
     assert [tuple(int(v) for v in p) for p in order(lib, pieces)] == model_order(pieces)
+
+
+@pytest.mark.parametrize("seqs, heads, chunk, pays", [
+    ([[4096]] * 8, 8, 512, False),                                       # two full rounds of equal items
+    ([[600]] * 40, 8, 1024, False),                                      # equal items, none of a chunk's length
+    ([[530, 562]] * 2, 4, 32, False),                                    # two 64-row drafts, 288 items of 32 keys
+    ([[100]] * 16, 8, 32, False),                                        # two rounds whatever the order
+    ([[1500]] * 8, 8, 512, False),                                       # less than a round
+    ([[16449]] * 2, 8, 512, True),                                       # a third round for 16 items of 65 keys
+    ([[int(n)] for n in np.random.default_rng(0).integers(1024, 8192, 16)], 8, 1024, True),
+    ([[64 * (i + 1) for i in range(32)]], 8, 1024, True),                # a 2048-row prefill chunk
+    ([[14336 + 64 * (i + 1) for i in range(32)]], 8, 2048, False),       # one deep in a prompt
+])
+def test_longest_first_only_where_it_shortens_the_launch(lib, seqs, heads, chunk, pays):
+    a = np.ascontiguousarray(pieces_of(seqs, heads, chunk), np.int32)
+    assert bool(lib.hvdh_attn_order_pays(len(a), a.ctypes.data_as(ctypes.c_void_p), 256)) == pays
